@@ -589,7 +589,9 @@ santa_status_t santa_plan_info(const santa_shape_t *shape, const santa_kv_t *kv,
     info->kernels = "k_row_flash";
   } else if (kind == SANTA_KIND_DENSE || kind == SANTA_KIND_FLASH) {
     info->path = SANTA_PATH_ONE_LAUNCH;
-    info->kernels = kind == SANTA_KIND_DENSE ? "k_fused_dense" : "k_fused_dense (flash mode)";
+    info->kernels = kind != SANTA_KIND_DENSE                            ? "k_fused_dense (flash mode)"
+                    : santa::dense_streams(p, kv->block_table != nullptr) ? "k_dense_stream"
+                                                                            : "k_fused_dense";
   } else if (p.rows) {
     info->path = SANTA_PATH_SCHEDULED;
     info->kernels = "k_row_sampled";

@@ -218,6 +218,266 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PERSIS
   }
 }
 
+// ---------------------------------------------------------------------------
+// Dense step of 16-bit and FP8 caches
+// ---------------------------------------------------------------------------
+// Lane `src` of every 16-lane row, on all lanes of the row.
+template <int SRC>
+__device__ __forceinline__ float row_bcast(float v) {
+  return dpp<0x150 + SRC>(v);
+}
+
+// Online softmax state of one wave: running maximum of head lane % 16 (log2
+// units), the lane's share of its sum, and the weighted V rows of the lane's
+// row slot (lane / 16), 8 columns of every head.
+template <int G>
+struct WaveSoftmax {
+  float m, l, acc[G][8];
+};
+
+// One tile of a wave: scores y (KeyRing::scores), then O += P V over the tile's
+// rows.  Lane (slot, c) adds rows 4 slot .. + 3, whose weights the lanes of its
+// own 16-lane row hold (head h in lane h): a row broadcast, no exchange
+// through LDS.  PART: only the first `left` keys count.
+template <typename E, int G, bool PART, typename R>
+__device__ __forceinline__ void dense_tile(const R &kr, mf32x4 y, int vslot, int left, WaveSoftmax<G> &w) {
+  const int lane = threadIdx.x & 63, r0 = 4 * (lane >> 4);
+  if constexpr (PART) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) y[n] = r0 + n < left ? y[n] : -kInf;
+  }
+  const float tm = xor32_max(xor16_max(fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3]))));
+  const float mn = fmaxf(w.m, tm);
+  const float ms = mn == -kInf ? 0.0f : mn;  // no finite score yet: every weight is 0
+  if (__any((lane & 15) < G && mn > w.m)) {
+    const float f = fast_exp2(w.m - ms);
+    w.l *= f;
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const float fh = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), h));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) w.acc[h][i] *= fh;
+    }
+    w.m = mn;
+  }
+  float p[4];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) p[n] = fast_exp2(y[n] - ms);
+  w.l += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    float f[8];
+    kr.row_chunk(r0 + n, vslot).to_float(f);
+    if constexpr (PART) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[i] = r0 + n < left ? f[i] : 0.0f;
+    }
+    auto head = [&](auto hc) {
+      constexpr int h = decltype(hc)::value;
+      if constexpr (h < G) {
+        const float pw = row_bcast<h>(p[n]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w.acc[h][i] = fmaf(pw, f[i], w.acc[h][i]);
+      }
+    };
+    head(std::integral_constant<int, 0>{});
+    head(std::integral_constant<int, 1>{});
+    head(std::integral_constant<int, 2>{});
+    head(std::integral_constant<int, 3>{});
+    head(std::integral_constant<int, 4>{});
+    head(std::integral_constant<int, 5>{});
+    head(std::integral_constant<int, 6>{});
+    head(std::integral_constant<int, 7>{});
+  }
+}
+
+// Pairs of tiles (16 keys, their 16 value rows) in a wave's ring: two, 64 KB
+// per workgroup (FP8: four of half the size), so two workgroups per CU.
+template <typename E>
+constexpr int dense_pairs() {
+  return sizeof(E) == 1 ? 4 : 2;
+}
+template <typename E>
+constexpr size_t dense_lds_bytes(int G, int T) {
+  const size_t ring = ring_bytes<E>(2 * dense_pairs<E>());
+  const size_t red = (size_t)4 * G * kHeadDim * 4, mrg = (size_t)G * T * 4;
+  return ring > red ? (ring > mrg ? ring : mrg) : (red > mrg ? red : mrg);
+}
+
+// The exact step (Sec. 2, SDPA equation), one workgroup per (row, split).  It is
+// bound by HBM: every key and value row is read once.  Each wave streams key and
+// value tiles in turn through its own ring in LDS (KeyRing) and keeps its own
+// online softmax, so nothing is exchanged and no barrier stands inside the
+// stream, and the value rows of a tile are in flight while its keys are
+// scored; the four waves are joined once at the end.  The split publishes o_t
+// = sum exp2(s - m_t) V and (m_t, l_t); the row's last arrival merges O =
+// sum_t a_t o_t / sum_t a_t l_t, a_t = exp2(m_t - m*).  24 ragged
+// paged sequences of 512 to 16384 keys with the append: 207.2 -> 170.3 us (4.5
+// -> 5.5 TB/s; k_fused_dense's append variant spills).  Without the V arithmetic
+// it takes 164 us, without the merge 162; rings of three pairs take 241 us:
+// more than about 64 KB per CU in flight only queues up.
+template <typename E, int G, bool PAGED, bool APPEND = false>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_dense_stream(FusedArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float dyn[];
+  constexpr int NP = dense_pairs<E>(), NB = 2 * NP;
+  __shared__ float wm[4][G], wl[4][G], mh[G], lh[G], den[G];
+  __shared__ int rank_lds;
+  const int T = a.T, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rowkv = blockIdx.x / T, t = blockIdx.x % T;
+  const int b = rowkv / a.Hkv, kvh = rowkv % a.Hkv;
+  const int64_t row0 = (int64_t)b * a.Hq + kvh * G;
+  QE<E> *out = static_cast<QE<E> *>(a.out);
+  const int L = seq_len(a.kv, b);
+  int Ls, Tb;
+  split_geometry(L, T, Ls, Tb);
+  if (Ls < a.Ls) {  // short rows take fewer splits of at least a.Ls keys, not T tiny ones
+    Ls = a.Ls;
+    Tb = (L + Ls - 1) / Ls;
+  }
+  if (t >= Tb) {
+    if (Tb == 0 && t == 0)  // empty sequence: zero output
+      for (int o = tid; o < G * kHeadDim; o += kThreads) store_out(out + row0 * kHeadDim + o, 0.0f);
+    return;
+  }
+  const int start = t * Ls, nrows = min(Ls, L - start);
+  if constexpr (APPEND) append_current<E, PAGED>(a.kv, b, kvh, a.Hkv, start, nrows, L);
+
+  WaveSoftmax<G> w;
+  w.m = -kInf;
+  w.l = 0.0f;
+#pragma unroll
+  for (int h = 0; h < G; ++h)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w.acc[h][i] = 0.0f;
+  const float2 sc = kv_scales<E>(a.kv, b, kvh, a.Hkv);  // FP8 cache: K and V scales
+  {
+    const QFrag qf = load_q_frag<E, G>(static_cast<const QE<E> *>(a.q), row0);
+    const float scale = a.scale_log2 * sc.x;
+    KeyRing<E, G, PAGED, NB> kr(a.kv, wave, reinterpret_cast<char *>(dyn));
+    const int mine = kr.item(b, start, nrows, page_window<PAGED>(a.kv, b, start, nrows));
+    constexpr int NL = KeyRing<E, G, PAGED, NB>::NL;
+    auto copy = [&](int i, int pair) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the pair's last reads are done
+      kr.copy(a.kv.k, kvh, i, 2 * pair);
+      kr.copy(a.kv.v, kvh, i, 2 * pair + 1);
+    };
+#pragma unroll
+    for (int i = 0; i < NP - 1; ++i)
+      if (i < mine) copy(i, i);
+    // the queries are complete, in the compiler's books too: it puts no wait
+    // of its own into the stream
+    __builtin_amdgcn_s_waitcnt(0);
+    int pair = 0, ahead = NP - 1;
+#pragma unroll 1
+    for (int i = 0; i < mine; ++i) {
+      const bool more = i + NP - 1 < mine;
+      if (more) {
+        copy(i + NP - 1, ahead);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((2 * NP - 1) * NL) : "memory");  // the keys have landed
+      } else {
+        wait_stores();
+      }
+      const mf32x4 y = kr.scores(qf, 2 * pair, scale);
+      if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((2 * NP - 2) * NL) : "memory");  // the value rows too
+      const int left = nrows - (wave + 4 * i) * kTileKeys;
+      if (left >= kTileKeys) dense_tile<E, G, false>(kr, y, 2 * pair + 1, left, w);
+      else dense_tile<E, G, true>(kr, y, 2 * pair + 1, left, w);
+      pair = pair + 1 == NP ? 0 : pair + 1;
+      ahead = ahead + 1 == NP ? 0 : ahead + 1;
+    }
+  }
+  // join the four waves: m_t, l_t, then o_t in wave order
+  const float l = xor32_sum(xor16_sum(w.l));
+  if (lane < G) wm[wave][lane] = w.m, wl[wave][lane] = l;
+  __syncthreads();
+  if (tid < G) {
+    const float m = fmaxf(fmaxf(wm[0][tid], wm[1][tid]), fmaxf(wm[2][tid], wm[3][tid]));
+    const float ms = m == -kInf ? 0.0f : m;
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float f = fast_exp2(wm[i][tid] - ms);
+      s = fmaf(f, wl[i][tid], s);
+      wm[i][tid] = f;
+    }
+    mh[tid] = m;
+    lh[tid] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const float f = wm[wave][h];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w.acc[h][i] *= f;
+  }
+  float *red = dyn;  // the rings are done with
+  reduce_slots<G>(w.acc, red);
+  unsigned long long *sync = a.sync + (int64_t)rowkv * (kSyncStride / 2);
+  const unsigned long long base = __hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  float *part_row = a.part + (int64_t)rowkv * T * G * kHeadDim;
+  float2 *mypart = reinterpret_cast<float2 *>(part_row + (int64_t)t * G * kHeadDim);
+  for (int o2 = tid; o2 < G * kHeadDim / 2; o2 += kThreads) {
+    float2 v = make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v.x += red[i * G * kHeadDim + 2 * o2];
+      v.y += red[i * G * kHeadDim + 2 * o2 + 1];
+    }
+    st_coherent(mypart + o2, v);
+  }
+  if (tid < G) st_coherent(a.stats + (row0 + tid) * T + t, make_float2(mh[tid], lh[tid]));
+
+  const int rank = row_arrive(sync, base, &rank_lds);
+  if (rank != Tb - 1) return;
+  if (tid == 0)
+    __hip_atomic_store(sync + 1, base + (unsigned long long)Tb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  float *al = dyn;  // [G][T]: a_t
+  for (int h = wave; h < G; h += kThreads / 64) {
+    const float2 *st = a.stats + (row0 + h) * T;
+    constexpr int CH = kMaxSplits / 64;
+    float2 v[CH];
+    float m = -kInf, d = 0.0f;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      v[i] = lane + 64 * i < Tb ? ld_coherent(st + lane + 64 * i) : make_float2(-kInf, 0.0f);
+      m = fmaxf(m, v[i].x);
+    }
+    m = wave_max(m);
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+      if (lane + 64 * i < Tb) {
+        const float at = fast_exp2(v[i].x - m);
+        al[h * T + lane + 64 * i] = at;
+        d = fmaf(at, v[i].y, d);
+      }
+    d = wave_sum(d);
+    if (lane == 0) den[h] = d;
+  }
+  __syncthreads();
+  for (int o2 = tid; o2 < G * kHeadDim / 2; o2 += kThreads) {  // column pairs; split order, 32 in flight
+    const int o = 2 * o2, h = o / kHeadDim;
+    float sx = 0.0f, sy = 0.0f;
+    constexpr int NV = 32;
+    for (int t0 = 0; t0 < Tb; t0 += NV) {
+      float2 v[NV];
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        v[i] = t0 + i < Tb ? ld_coherent(reinterpret_cast<const float2 *>(part_row + (int64_t)(t0 + i) * G * kHeadDim + o))
+                           : make_float2(0.0f, 0.0f);
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (t0 + i < Tb) {
+          const float at = al[h * T + t0 + i];
+          sx = fmaf(at, v[i].x, sx);
+          sy = fmaf(at, v[i].y, sy);
+        }
+    }
+    store_out(out + row0 * kHeadDim + o, sx * sc.y / den[h]);
+    store_out(out + row0 * kHeadDim + o + 1, sy * sc.y / den[h]);
+  }
+}
+
 template <typename E>
 hipError_t launch_dense_e(const Plan &p, const KvView &kv, const void *q, float scale_log2,
                           void *out, char *ws, hipStream_t st) {
@@ -225,8 +485,20 @@ hipError_t launch_dense_e(const Plan &p, const KvView &kv, const void *q, float 
   return with_g_paged(p.G, kv.bt != nullptr, [&](auto gc, auto paged) -> hipError_t {
     constexpr int G = decltype(gc)::value;
     constexpr bool PG = decltype(paged)::value;
-    const size_t lds = (size_t)fused_dense_floats(G, kSplitMax, p.T) * 4;
     const bool ap = kv.k_new != nullptr;
+    if constexpr (sizeof(E) <= 2) {
+      if (dense_streams(p, PG)) {
+        args.Ls = std::min(p.Ls, 512);
+        const void *fn = reinterpret_cast<const void *>(&k_dense_stream<E, G, PG>);
+        if constexpr (sizeof(E) == 2)  // (an FP8 cache takes no append)
+          if (ap) fn = reinterpret_cast<const void *>(&k_dense_stream<E, G, PG, true>);
+        void *params[] = {&args};
+        const CallTimer tm = call_timer();
+        return hipExtLaunchKernel(fn, dim3(p.B * p.Hkv * p.T), dim3(kThreads), params,
+                                  dense_lds_bytes<E>(G, p.T), st, tm.start, tm.stop, 0);
+      }
+    }
+    const size_t lds = (size_t)fused_dense_floats(G, kSplitMax, p.T) * 4;
     const void *res = ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true, false, true>)
                          : reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true>);
     const int rows = p.B * p.Hkv;

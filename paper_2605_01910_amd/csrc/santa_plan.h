@@ -66,6 +66,19 @@ struct Plan {
   size_t total;
 };
 
+// The dense step of 16-bit and FP8 caches takes k_dense_stream on grids (KV
+// rows x splits) of several workgroups per CU, where its continuous stream
+// counts (us, this kernel / k_fused_dense, 32k keys unless said): batch 4 98.9
+// / 112.4, batch 16 350 / 374, head-major 344 / 351, FP8 227 / 238, groups of
+// 8 at batch 4 114 / 147, 24 ragged paged sequences up to 16k 175 / 210.  At
+// two workgroups per CU a contiguous cache streams as fast through registers
+// and the deeper rings only queue up (batch 1 34.7 / 30.4, batch 2 55.1 / 52.1,
+// batch 8 at 8k 54.2 / 50.7); a paged one does not (4 ragged sequences up to
+// 9000 keys 23.9 / 31.7).
+inline bool dense_streams(const Plan &p, bool paged) {
+  return p.elem != 1 && (int64_t)p.B * p.Hkv * p.T > (paged ? 256 : 512);
+}
+
 // KV cache as the kernels see it (see santa_kv_t for the addressing rules).
 struct KvView {
   const void *k, *v;

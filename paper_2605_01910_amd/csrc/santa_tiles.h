@@ -12,6 +12,10 @@ namespace santa {
 // ---------------------------------------------------------------------------
 // shared device pieces
 // ---------------------------------------------------------------------------
+// Wait until this wave's outstanding memory operations have completed; also a
+// compiler barrier for memory accesses.
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // The G query rows of a KV group, 8 features per lane, in the query element
 // type QE<E> (bfloat16 for an FP8 cache).
 template <typename E, int G>
@@ -103,6 +107,22 @@ __device__ __forceinline__ int64_t row16_offset(const KvView &kv, const PageWin 
            (int64_t)kvh * kv.sh;
   } else {
     return (int64_t)b * kv.sb + (int64_t)row0 * kv.sn + (int64_t)kvh * kv.sh;
+  }
+}
+
+// Element offset of token pos (feature 0) of the split whose page window is
+// pw, for lane-varying positions; every lane of the wave calls it (the page
+// comes from the lane that holds its entry), valid only where ok.
+template <bool PAGED>
+__device__ __forceinline__ int64_t row_offset_win(const KvView &kv, const PageWin &pw, int b, int kvh,
+                                                  int pos, bool ok) {
+  if constexpr (PAGED) {
+    if (kv.ps_log2 < 4) return ok ? row_offset<true>(kv, b, kvh, pos) : 0;
+    const int page = __shfl(pw.entry, (pos >> kv.ps_log2) - pw.p0);
+    return (int64_t)page * kv.sb + (int64_t)(pos & ((1 << kv.ps_log2) - 1)) * kv.sn +
+           (int64_t)kvh * kv.sh;
+  } else {
+    return row_offset<false>(kv, b, kvh, pos);
   }
 }
 
@@ -260,6 +280,220 @@ __device__ __forceinline__ void score_tile(const KvView &kv, int b, int kvh, int
     for (int h = 0; h < G; ++h) mx[h] = h == hq ? m1 : -kInf;
   }
 }
+
+// ---------------------------------------------------------------------------
+// Matrix-core score tile (16-bit and FP8 caches)
+// ---------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef float mf32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int mu32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void *lds_ptr_t;
+
+constexpr int kTileKeys = 16;  // keys per tile: one matrix instruction's rows
+// Bytes of one tile of key rows, and of the ring of NB tiles that each wave
+// of the workgroup streams its keys through.
+template <typename E>
+constexpr int tile_bytes() {
+  return kTileKeys * kHeadDim * (int)sizeof(E);
+}
+template <typename E>
+constexpr int ring_bytes(int nb) {
+  return (kThreads / 64) * nb * tile_bytes<E>();
+}
+
+// LDS byte address of a generic pointer into LDS.
+__device__ __forceinline__ unsigned lds_addr(const void *p) {
+  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
+}
+
+// First of the 8 features that lane group g (lane / 16) holds of a key in step
+// s (0..3) of the 128-feature dot product.  Any assignment works as long as
+// keys and queries agree; these follow the 16-byte chunks that the keys are
+// read from LDS in (bf16: one chunk per step; FP8: one chunk per two steps).
+template <typename E>
+__device__ __forceinline__ int frag_feature(int g, int s) {
+  return sizeof(E) == 1 ? 16 * (g + 4 * (s >> 1)) + 8 * (s & 1) : 32 * s + 8 * g;
+}
+
+// The G queries of a KV group as the B operand of v_mfma_f32_16x16x32_bf16:
+// lane l holds features frag_feature(l / 16, s) .. + 7 of head l % 16, zero
+// for columns past G.
+struct QFrag {
+  bf16x8_t s[4];
+};
+template <typename E, int G>
+__device__ __forceinline__ QFrag load_q_frag(const QE<E> *q, int64_t row0) {
+  static_assert(sizeof(QE<E>) == 2, "bfloat16 queries");
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  QFrag f;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    mu32x4 v = {0u, 0u, 0u, 0u};
+    if (n < G) v = *reinterpret_cast<const mu32x4 *>(q + (row0 + n) * kHeadDim + frag_feature<E>(g, s));
+    f.s[s] = __builtin_bit_cast(bf16x8_t, v);
+  }
+  return f;
+}
+
+// Scores of the four rows this lane group holds, from the tile at LDS byte
+// addresses ro[]: D = K Q^T, lane l: keys 4 (l/16) .. + 3 of head l % 16.
+template <typename E>
+__device__ __forceinline__ mf32x4 score_frag(const QFrag &qf, const unsigned (&ro)[4], unsigned off) {
+  mf32x4 d = {0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (sizeof(E) == 2) {
+    mu32x4 a[4];
+    asm volatile(
+        "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\t"
+        "ds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
+        : "v"(ro[0] + off), "v"(ro[1] + off), "v"(ro[2] + off), "v"(ro[3] + off)
+        : "memory");
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[s]), qf.s[s], d, 0, 0, 0);
+  } else {
+    mu32x4 a[2];
+    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(a[0]), "=&v"(a[1])
+                 : "v"(ro[0] + off), "v"(ro[1] + off)
+                 : "memory");
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const Chunk<uint8_t> ch{make_uint2(a[s >> 1][2 * (s & 1)], a[s >> 1][2 * (s & 1) + 1])};
+      d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ch.to_bf16()), qf.s[s], d,
+                                                  0, 0, 0);
+    }
+  }
+  return d;
+}
+
+// A wave's key stream through its ring in LDS, scored on the matrix cores
+// (Sec. 2, SDPA equation, the q K^T product).
+//
+// Wave w of the workgroup's four takes the 16-key tiles w, w + 4, ... of the
+// split.  A tile's rows are copied straight from memory into the wave's own
+// ring of NB tiles in LDS (loads with the lds modifier: 16 bytes per lane, no
+// registers held), NB - 1 tiles ahead of the one that is scored; no workgroup
+// barrier is needed.  Whole rows are read by consecutive lanes, and the
+// 16-byte chunks of a row are permuted by an XOR with its row number on the
+// way (row r keeps chunk c at position c ^ r; FP8, 8 chunks: c ^ (r / 2)), so
+// that the operand reads -- 16 lanes, the same chunk of 16 rows -- meet every
+// LDS bank once.  The register form of the stream (score_tile: 16 lanes per
+// row, four dot2 per head and a 16-lane reduction) needs about 30 vector
+// instructions per 4 keys at G = 4 and 90 at G = 8; here 16 keys take 4 matrix
+// instructions and about 15 others, whatever G is.  Reading 1 GiB of keys in
+// 1024-key splits: 160 us so, 171 us for the register form's loads alone, 200
+// us for loads straight into the operand layout (64-byte pieces of rows).
+// Rows past the end of the split repeat its last row, so they change no
+// maximum; their scores land in entries at or past nrows.
+// The copies are inline assembly: the compiler would otherwise wait for all of
+// them before any other LDS access of the wave.
+template <typename E, int G, bool PAGED, int NB>
+struct KeyRing {
+  static constexpr int TB = tile_bytes<E>(), NL = TB / 1024;  // copies per tile (1 KiB each)
+  static constexpr int CPR = kHeadDim * (int)sizeof(E) / 16;   // 16-byte chunks per row: 16 or 8
+  static constexpr int RPL = 64 / CPR;                         // rows per copy
+  const KvView &kv;
+  int b = 0, start = 0, nrows = 0, wave;
+  PageWin pw{0, 0};
+  char *my;          // the wave's ring
+  uint32_t vo[NL];   // byte offsets of the lane's copies in a whole tile
+  unsigned ro[4];    // LDS addresses of the lane's operand chunks in the ring's first tile
+
+  __device__ __forceinline__ int row_of(int n) const { return n * RPL + (threadIdx.x & 63) / CPR; }
+  __device__ __forceinline__ int chunk_at(int row) const {
+    const int p = (threadIdx.x & 63) % CPR;
+    return sizeof(E) == 1 ? p ^ (row >> 1) : p ^ row;
+  }
+  // w: this wave's number among the four streaming waves (wave-uniform)
+  __device__ __forceinline__ KeyRing(const KvView &kv_, int w, char *ring) : kv(kv_), wave(w) {
+    my = ring + w * NB * TB;
+#pragma unroll
+    for (int n = 0; n < NL; ++n)
+      vo[n] = (uint32_t)((int64_t)row_of(n) * kv.sn * (int64_t)sizeof(E)) + chunk_at(row_of(n)) * 16;
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const unsigned rb = lds_addr(my) + r * (CPR * 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      ro[i] = rb + (sizeof(E) == 1 ? ((g + 4 * (i & 1)) ^ (r >> 1)) : ((4 * i + g) ^ r)) * 16;
+  }
+  // The split whose tiles are copied from here on; returns this wave's tiles.
+  __device__ __forceinline__ int item(int b_, int start_, int nrows_, const PageWin &pw_) {
+    b = b_;
+    start = start_;
+    nrows = nrows_;
+    pw = pw_;
+    const int nt = (nrows + kTileKeys - 1) / kTileKeys;
+    return wave < nt ? (nt - wave + 3) >> 2 : 0;
+  }
+
+  // Start copying the wave's tile i of KV head kvh of the cache `base` (kv.k or
+  // kv.v) into ring slot `slot`.
+  __device__ __forceinline__ void copy(const void *base, int kvh, int i, int slot) const {
+    const E *K = static_cast<const E *>(base);
+    const int tile = wave + 4 * i, left = nrows - tile * kTileKeys;
+    char *dst = my + slot * TB;
+    const unsigned m = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_addr(dst));
+    if constexpr (PAGED) {
+      if (kv.ps_log2 < 4) {  // pages of fewer than 16 keys: one lookup per row
+#pragma unroll
+        for (int n = 0; n < NL; ++n) {
+          const int row = row_of(n);
+          const char *r = reinterpret_cast<const char *>(
+                              K + row_offset<true>(kv, b, kvh, start + tile * kTileKeys + min(row, left - 1))) +
+                          chunk_at(row) * 16;
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                       ::"s"(m + n * 1024u), "v"(r)
+                       : "memory", "m0");
+        }
+        return;
+      }
+    }
+    const E *p = K + row16_offset<PAGED>(kv, pw, b, kvh, start + tile * kTileKeys);
+    uint32_t o[NL];
+#pragma unroll
+    for (int n = 0; n < NL; ++n) {
+      o[n] = vo[n];
+      if (left < kTileKeys)
+        o[n] = (uint32_t)((int64_t)min(row_of(n), left - 1) * kv.sn * (int64_t)sizeof(E)) + chunk_at(row_of(n)) * 16;
+    }
+    // buffer resource over p (uniform): base, no range limit, raw format
+    const uint64_t pa = (uint64_t)(uintptr_t)p;
+    const mu32x4 rs = {(unsigned)__builtin_amdgcn_readfirstlane((int)pa),
+                       (unsigned)__builtin_amdgcn_readfirstlane((int)(pa >> 32)) & 0xffffu, 0x7fffffffu, 0x00020000u};
+    if constexpr (NL == 4)
+      asm volatile(
+          "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %1, 0 offen nt lds\n\t"
+          "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %1, 0 offen nt lds\n\t"
+          "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %4, %1, 0 offen nt lds\n\t"
+          "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %5, %1, 0 offen nt lds"
+          ::"s"(m), "s"(rs), "v"(o[0]), "v"(o[1]), "v"(o[2 % NL]), "v"(o[3 % NL])
+          : "memory", "m0", "scc");
+    else
+      asm volatile(
+          "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %1, 0 offen nt lds\n\t"
+          "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %1, 0 offen nt lds"
+          ::"s"(m), "s"(rs), "v"(o[0]), "v"(o[1])
+          : "memory", "m0", "scc");
+  }
+
+  // Scaled scores of the tile in ring slot `slot`: lane l holds keys 4 (l/16) ..
+  // + 3 of head l % 16.
+  __device__ __forceinline__ mf32x4 scores(const QFrag &qf, int slot, float scale_log2) const {
+    mf32x4 y = score_frag<E>(qf, ro, slot * TB);
+    y *= scale_log2;
+    return y;
+  }
+
+  // Features 8c .. 8c + 7 (c = lane % 16) of row `row` of the tile in ring slot
+  // `slot`, as the copies laid it out.
+  __device__ __forceinline__ Chunk<E> row_chunk(int row, int slot) const {
+    const char *t = my + slot * TB + row * (CPR * 16);
+    const int c = threadIdx.x & 15;
+    if constexpr (sizeof(E) == 2) return Chunk<E>::load(reinterpret_cast<const E *>(t + ((c ^ row) & 15) * 16));
+    else return Chunk<E>::load(reinterpret_cast<const E *>(t + (((c >> 1) ^ (row >> 1)) & 7) * 16 + (c & 1) * 8));
+  }
+};
 
 // Value tile of the exact decode (Sec. 2, SDPA equation, the weighted sum of
 // V): acc[h][i] = sum_j w[h*pitch + j] * V_{start+j}[8c + i] over the rows j
@@ -485,10 +719,6 @@ __device__ __forceinline__ void st_coherent(int *p, int v) {
 __device__ __forceinline__ int ld_coherent(const int *p) {
   return __hip_atomic_load(const_cast<int *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Wait until this wave's outstanding memory operations have completed; also a
-// compiler barrier for memory accesses.
-__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 // Fused current-token append (App. Decode-Step Kernel Microbenchmark Details,
 // note on KV-cache appends: the decode step stores the new token's key and
 // value before attending).  When kv.k_new is set, the workgroup whose split
