@@ -356,12 +356,14 @@ __attribute__((amdgpu_waves_per_eu(row_waves<E, G, PAGED>()))) void k_row_sample
   if constexpr (APPEND) append_current<E, PAGED>(a.kv, b, kvh, a.Hkv, start, nrows, L);
 
   // 1. scores of the G heads into LDS, split max, split CDF and statistics
-  {
+  const float ksc = kv_scales<E>(a.kv, b, kvh, a.Hkv).x;  // FP8 cache: K scale
+  if constexpr (ring_scored<E, G, PAGED>()) {
+    ring_scores<E, G, PAGED>(a.kv, b, kvh, start, nrows, static_cast<const QE<E> *>(a.q), row0,
+                             a.scale_log2 * ksc, P, pitch, P + G * pitch, mtmp, mh);
+  } else {
     const QRegs<E, G> qr = load_q<E, G>(static_cast<const QE<E> *>(a.q), b, a.Hq, kvh, tid & 15);
-    const float ksc = kv_scales<E>(a.kv, b, kvh, a.Hkv).x;  // FP8 cache: K scale
     float mx[G];
-    score_tile<E, G, PAGED, 4>(a.kv, b, kvh, start, nrows, qr,
-                                                    a.scale_log2 * ksc, P, pitch, mx);
+    score_tile<E, G, PAGED, 4>(a.kv, b, kvh, start, nrows, qr, a.scale_log2 * ksc, P, pitch, mx);
     block_max_heads<G>(mx, mtmp, mh);
   }
   // the row's counter base: it moves on only after every split of the row,
@@ -671,7 +673,7 @@ hipError_t launch_rows_e(const Plan &p, const KvView &kv, const void *q, float s
     // direct grids of G = 4 merge through LDS (merge_group4_lds: T partials,
     // at most 128 KiB, within the 160 KiB of a CU); staged stratified
     // uniforms (at most 2048 per head) follow the split CDFs
-    const size_t lds = std::max({(size_t)G * kSplitMax * 4,
+    const size_t lds = std::max({(size_t)G * kSplitMax * 4 + ring_scored_bytes<E, G, PG>(),
                                  args.direct && G == 4 ? (size_t)p.T * G * kHeadDim * 4 : 0,
                                  args.ustage ? (size_t)G * (kSplitMax + p.S) * 4 : 0});
     const CallTimer tm = call_timer();

@@ -85,14 +85,19 @@ __device__ __forceinline__ void stream_cdf_item(const FusedArgs &a, int rowkv, i
   const int start = t * Ls, nrows = min(Ls, L - start);
   if constexpr (APPEND) append_current<E, PAGED>(a.kv, b, kvh, a.Hkv, start, nrows, L);
 
-  const QRegs<E, G> qr = load_q<E, G>(static_cast<const QE<E> *>(a.q), b, a.Hq, kvh, tid & 15);
   const float ksc = kv_scales<E>(a.kv, b, kvh, a.Hkv).x;  // FP8 cache: K scale
-  float mx[G];
-  // 4 rows per lane and batch: this kernel relies on many resident waves
-  // (64 VGPRs) rather than on deep per-wave buffering
-  score_tile<E, G, PAGED, sizeof(E) == 1 ? 8 : 4>(a.kv, b, kvh, start, nrows, qr, a.scale_log2 * ksc,
-                                                  P, pitch, mx);
-  block_max_heads<G>(mx, mtmp, mh);
+  if constexpr (ring_scored<E, G, PAGED>()) {
+    ring_scores<E, G, PAGED>(a.kv, b, kvh, start, nrows, static_cast<const QE<E> *>(a.q), row0,
+                             a.scale_log2 * ksc, P, pitch, P + G * pitch, mtmp, mh);
+  } else {
+    const QRegs<E, G> qr = load_q<E, G>(static_cast<const QE<E> *>(a.q), b, a.Hq, kvh, tid & 15);
+    float mx[G];
+    // 4 rows per lane and batch: this kernel relies on many resident waves
+    // (64 VGPRs) rather than on deep per-wave buffering
+    score_tile<E, G, PAGED, sizeof(E) == 1 ? 8 : 4>(a.kv, b, kvh, start, nrows, qr, a.scale_log2 * ksc,
+                                                    P, pitch, mx);
+    block_max_heads<G>(mx, mtmp, mh);
+  }
   for (int h = wave; h < G; h += kThreads / 64) wave_split_cdf_m(P + h * pitch, nrows, lane, mh[h]);
   __syncthreads();
   write_split_stash<G>(a, P, mh, nrows, row0, t, start);
@@ -479,7 +484,7 @@ hipError_t launch_two_launch_e(const Plan &p, const KvView &kv, const void *q, f
     constexpr bool PG = decltype(paged)::value;
     const CallTimer tm = call_timer();
     void *params[] = {&args};
-    const size_t lds1 = (size_t)G * kSplitMax * 4;
+    const size_t lds1 = (size_t)G * kSplitMax * 4 + ring_scored_bytes<E, G, PG>();
     hipError_t e = hipExtLaunchKernel(kv.k_new ? reinterpret_cast<const void *>(&k_stream_cdf<E, G, PG, true>)
                                                : reinterpret_cast<const void *>(&k_stream_cdf<E, G, PG>),
                                       dim3(p.B * p.Hkv * p.T), dim3(kThreads), params, lds1, st,

@@ -587,6 +587,72 @@ __device__ __forceinline__ void block_max_heads(float (&mx)[G], float *tmp, floa
   __syncthreads();
 }
 
+// Whether the sampled steps' key stream goes through the matrix cores
+// (ring_scores) rather than through registers (score_tile): groups of eight,
+// where score_tile needs 90 vector instructions per 4 keys, and paged 16-bit
+// caches, whose page lookups leave score_tile half the waves of a contiguous
+// stream.  6 ragged paged sequences up to 20011 keys, G = 8, S = 1000: 93.0 ->
+// 89.5 us; 64 up to 65536 keys, G = 4: 924 -> 917 us (5.8 TB/s).  Contiguous
+// caches of smaller groups keep score_tile at eight waves per SIMD (batch 16 at
+// 32k: 187 us, 5.8 TB/s), which holds as many loads in flight as the rings.
+template <typename E, int G, bool PAGED>
+constexpr bool ring_scored() {
+  return sizeof(E) <= 2 && (G == 8 || (PAGED && sizeof(E) == 2));
+}
+// Tiles of each wave's ring: 32 KB per workgroup, so that it and the scores of
+// G heads leave room for two (G = 8) or three workgroups per CU.
+template <typename E>
+constexpr int score_tiles() {
+  return sizeof(E) == 1 ? 4 : 2;
+}
+template <typename E, int G, bool PAGED>
+constexpr size_t ring_scored_bytes() {
+  if constexpr (ring_scored<E, G, PAGED>()) return ring_bytes<E>(score_tiles<E>());
+  return 0;
+}
+
+// The score tile on the matrix cores: s[h*pitch + j] = scale_log2 * <q_h,
+// K_{start+j}> for j < nrows (entries up to the next multiple of 16 repeat the
+// last key's), and every head's maximum over the split in mh[h].  ring: each
+// wave's tiles in LDS, 16-byte aligned, apart from s; tmp: 4*G floats.
+template <typename E, int G, bool PAGED>
+__device__ __forceinline__ void ring_scores(const KvView &kv, int b, int kvh, int start, int nrows,
+                                            const QE<E> *q, int64_t row0, float scale_log2, float *s,
+                                            int pitch, void *ring, float *tmp, float *mh) {
+  constexpr int NB = score_tiles<E>();
+  using Ring = KeyRing<E, G, PAGED, NB>;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const QFrag qf = load_q_frag<E, G>(q, row0);
+  Ring kr(kv, wave, static_cast<char *>(ring));
+  const int mine = kr.item(b, start, nrows, page_window<PAGED>(kv, b, start, nrows));
+#pragma unroll
+  for (int i = 0; i < NB - 1; ++i)
+    if (i < mine) kr.copy(kv.k, kvh, i, i);
+  __builtin_amdgcn_s_waitcnt(0);  // the queries, in the compiler's books too
+  float m = -kInf;
+  int slot = 0, ahead = NB - 1;
+#pragma unroll 1
+  for (int i = 0; i < mine; ++i) {
+    if (i + NB - 1 < mine) {  // (the slot's operand reads ended in score_frag)
+      kr.copy(kv.k, kvh, i + NB - 1, ahead);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 1) * Ring::NL) : "memory");
+    } else {
+      wait_stores();
+    }
+    const mf32x4 y = kr.scores(qf, slot, scale_log2);
+    m = fmaxf(fmaxf(m, fmaxf(y[0], y[1])), fmaxf(y[2], y[3]));
+    if (h < G) *reinterpret_cast<mf32x4 *>(s + h * pitch + (wave + 4 * i) * kTileKeys + 4 * g) = y;
+    slot = slot + 1 == NB ? 0 : slot + 1;
+    ahead = ahead + 1 == NB ? 0 : ahead + 1;
+  }
+  m = xor32_max(xor16_max(m));
+  if (lane < G) tmp[wave * G + lane] = m;
+  __syncthreads();
+  if (tid < G) mh[tid] = fmaxf(fmaxf(tmp[tid], tmp[G + tid]), fmaxf(tmp[2 * G + tid], tmp[3 * G + tid]));
+  __syncthreads();
+}
+
 // Split-local CDF of one head, computed by one wave (Sec. 2.1, "Construction":
 // F is the running sum of the attention weights).  On return s[j] holds
 // P_j = sum_{i<=j} exp2(s_i - m) for j < nrows (nrows <= kSplitMax; s has room

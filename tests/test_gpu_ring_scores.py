@@ -1,0 +1,40 @@
+"""The sampled steps' matrix-core score stage (ring_scores) at the edges of its 16-key tiles and
+splits, against the CPU oracle: rows of 0 keys, of one key, of a tile plus or minus one, fewer
+tiles than waves, splits longer than the ring; pages of 4 to 64 keys, and groups of eight query
+heads on every cache.  What lies past a row's length is NaN: none of it may reach the output.
+Each of a key's 128 products is exact in float32 and their order of summation is all that differs
+between score stages, so the indices keep the oracle's 1e-5 band."""
+
+import numpy as np
+import pytest
+
+from paper_2605_01910_amd import santa as S
+from tests.gpu_util import DeviceWorkload, KIND_CODE, check_sampled, log, run
+from tests.test_gpu_dense_stream import _poison
+from workload import make_workload
+
+pytestmark = pytest.mark.gpu
+
+LENS = [0, 1, 15, 16, 17, 63, 65, 1023, 1024, 1025, 2600]
+
+
+@pytest.mark.parametrize("kind", ["systematic", "stratified"])
+@pytest.mark.parametrize("path,kernels", [("rows", "k_row_sampled"), ("two", "k_stream_cdf")])
+@pytest.mark.parametrize("cache,G", [("page4", 4), ("page16", 1), ("page16", 2), ("page16", 4), ("page64", 4),
+                                     ("page4", 8), ("page16", 8), ("bf16", 8), ("fp8", 8), ("fp8page16", 8)])
+def test_ring_scores_edges(cache, G, path, kernels, kind):
+    over = dict(B=len(LENS), Hkv=2, Hq=2 * G, n=max(LENS), ctx_len=LENS, kind=kind, S=40)
+    if cache.startswith("fp8"):
+        over["kv_dtype"] = "fp8"
+    if "page" in cache:
+        over.update(paged=True, page_size=int(cache.split("page")[1]))
+    w = make_workload(2, seed=79, **over)
+    dw = DeviceWorkload(w)
+    _poison(dw, w)
+    with S.options(path, splits=3):
+        plan = S.santa_plan_info(dw.shape, dw.kv, w.S, KIND_CODE[kind])
+        assert kernels in plan["kernels"], plan
+        out, idx, _ = run(w, dw=dw)
+        again, idx2, _ = run(w, dw=dw)
+    assert np.array_equal(out, again) and np.array_equal(idx, idx2)
+    log(f"[ring scores {cache} G={G} {path} {kind}] {check_sampled(w, out, idx)}")
