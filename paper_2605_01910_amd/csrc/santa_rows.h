@@ -250,8 +250,19 @@ __device__ __forceinline__ void row_head_value(const FusedArgs &a, const HeadCla
     rlo = __builtin_amdgcn_readlane(n, 0);
     rhi = __builtin_amdgcn_readlane(n, 1);
   }
+  // two heads per wave (G = 8): the uniforms are in memory, and each pass of 64
+  // claims fetches the next pass's, so that their latency runs under this
+  // pass's searches and gathers (6 ragged paged sequences up to 20011 keys, S =
+  // 1000: 92.9 -> 91.4 us; 16 of them: 192.4 -> 188.6 us, cold 251 -> 244)
+  const bool fetch = MODE == kStrat && !staged;
+  float unext = 0.0f;
+  if (fetch && rlo + lane < rhi) unext = uh[rlo + lane];
   auto claim = [&](int r, bool ok) {
     float ur = ureg[0];
+    if (fetch) {
+      ur = unext;
+      if (r + 64 < rhi) unext = uh[r + 64];
+    }
     if (MODE != kSys && regs) {  // u_r (T_r) from lane r % 64 (every lane takes part)
       const int src = r & 63, k = (r >> 6) & 3;
       const float v0 = __shfl(ureg[0], src), v1 = __shfl(ureg[1], src);
@@ -261,7 +272,7 @@ __device__ __forceinline__ void row_head_value(const FusedArgs &a, const HeadCla
     int j = 0;
     if (ok) {
       const float tau = MODE == kIid ? (regs ? ur : uh[r]) * c.Z
-                                     : threshold(r, (MODE == kStrat && !regs) ? uh[r] : ur,
+                                     : threshold(r, (MODE == kStrat && !regs && !fetch) ? uh[r] : ur,
                                                  a.invS, c.Z);
       const int pos = lds_cdf_count(Ph, nrows, c.a, tau - c.lo);
       j = pos < nrows ? pos : nrows - 1;
