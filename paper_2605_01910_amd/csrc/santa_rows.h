@@ -368,7 +368,7 @@ __attribute__((amdgpu_waves_per_eu(row_waves<E, G, PAGED>()))) void k_row_sample
 
   // 1. scores of the G heads into LDS, split max, split CDF and statistics
   const float ksc = kv_scales<E>(a.kv, b, kvh, a.Hkv).x;  // FP8 cache: K scale
-  if constexpr (ring_scored<E, G, PAGED>()) {
+  if constexpr (ring_scored_rows<E, G, PAGED>()) {
     ring_scores<E, G, PAGED>(a.kv, b, kvh, start, nrows, static_cast<const QE<E> *>(a.q), row0,
                              a.scale_log2 * ksc, P, pitch, P + G * pitch, mtmp, mh);
   } else {
@@ -684,7 +684,7 @@ hipError_t launch_rows_e(const Plan &p, const KvView &kv, const void *q, float s
     // direct grids of G = 4 merge through LDS (merge_group4_lds: T partials,
     // at most 128 KiB, within the 160 KiB of a CU); staged stratified
     // uniforms (at most 2048 per head) follow the split CDFs
-    const size_t lds = std::max({(size_t)G * kSplitMax * 4 + ring_scored_bytes<E, G, PG>(),
+    const size_t lds = std::max({(size_t)G * kSplitMax * 4 + score_ring_bytes<E>(ring_scored_rows<E, G, PG>()),
                                  args.direct && G == 4 ? (size_t)p.T * G * kHeadDim * 4 : 0,
                                  args.ustage ? (size_t)G * (kSplitMax + p.S) * 4 : 0});
     const CallTimer tm = call_timer();

@@ -86,7 +86,7 @@ __device__ __forceinline__ void stream_cdf_item(const FusedArgs &a, int rowkv, i
   if constexpr (APPEND) append_current<E, PAGED>(a.kv, b, kvh, a.Hkv, start, nrows, L);
 
   const float ksc = kv_scales<E>(a.kv, b, kvh, a.Hkv).x;  // FP8 cache: K scale
-  if constexpr (ring_scored<E, G, PAGED>()) {
+  if constexpr (ring_scored<E, G>()) {
     ring_scores<E, G, PAGED>(a.kv, b, kvh, start, nrows, static_cast<const QE<E> *>(a.q), row0,
                              a.scale_log2 * ksc, P, pitch, P + G * pitch, mtmp, mh);
   } else {
@@ -484,7 +484,7 @@ hipError_t launch_two_launch_e(const Plan &p, const KvView &kv, const void *q, f
     constexpr bool PG = decltype(paged)::value;
     const CallTimer tm = call_timer();
     void *params[] = {&args};
-    const size_t lds1 = (size_t)G * kSplitMax * 4 + ring_scored_bytes<E, G, PG>();
+    const size_t lds1 = (size_t)G * kSplitMax * 4 + score_ring_bytes<E>(ring_scored<E, G>());
     hipError_t e = hipExtLaunchKernel(kv.k_new ? reinterpret_cast<const void *>(&k_stream_cdf<E, G, PG, true>)
                                                : reinterpret_cast<const void *>(&k_stream_cdf<E, G, PG>),
                                       dim3(p.B * p.Hkv * p.T), dim3(kThreads), params, lds1, st,

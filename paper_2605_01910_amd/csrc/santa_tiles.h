@@ -593,17 +593,27 @@ __device__ __forceinline__ void block_max_heads(float (&mx)[G], float *tmp, floa
   __syncthreads();
 }
 
-// Whether the sampled steps' key stream goes through the matrix cores
-// (ring_scores) rather than through registers (score_tile): groups of eight,
-// where score_tile needs 90 vector instructions per 4 keys, and paged 16-bit
-// caches, whose page lookups leave score_tile half the waves of a contiguous
-// stream.  6 ragged paged sequences up to 20011 keys, G = 8, S = 1000: 93.0 ->
-// 89.5 us; 64 up to 65536 keys, G = 4: 924 -> 917 us (5.8 TB/s).  Contiguous
-// caches of smaller groups keep score_tile at eight waves per SIMD (batch 16 at
-// 32k: 187 us, 5.8 TB/s), which holds as many loads in flight as the rings.
-template <typename E, int G, bool PAGED>
+// Whether a sampled step's key stream goes through the matrix cores
+// (ring_scores) rather than through registers (score_tile) on every grid:
+// groups of eight, where score_tile needs 90 vector instructions per 4 keys
+// and 143 registers (us, score_tile / ring_scores, S = 256, 32k keys: batch 1
+// contiguous 40.7 / 29.9, paged 48.6 / 30.8, FP8 41.2 / 27.7; batch 16 296 /
+// 279, 352 / 297, FP8 263 / 139).
+template <typename E, int G>
 constexpr bool ring_scored() {
-  return sizeof(E) <= 2 && (G == 8 || (PAGED && sizeof(E) == 2));
+  return sizeof(E) <= 2 && G == 8;
+}
+// The scheduled kernel (k_row_sampled) also scores paged 16-bit caches of
+// smaller groups so: their page lookups leave score_tile half the waves of a
+// contiguous stream (batch 1, G = 4, 32k keys: 25.0 / 18.5 us).  The two-launch
+// stream of these keeps score_tile: 64 sequences up to 65536 keys gain 0.5 to
+// 1.4 % (G = 1 to 4), less than it is worth to have a paged cache draw other
+// keys, at ties of rounding, than a contiguous one.  Contiguous caches of
+// smaller groups keep score_tile at eight waves per SIMD (batch 16 at 32k: 187
+// us, 5.8 TB/s), which holds as many loads in flight as the rings.
+template <typename E, int G, bool PAGED>
+constexpr bool ring_scored_rows() {
+  return ring_scored<E, G>() || (PAGED && sizeof(E) == 2);
 }
 // Tiles of each wave's ring: 32 KB per workgroup, so that it and the scores of
 // G heads leave room for two (G = 8) or three workgroups per CU.
@@ -611,10 +621,10 @@ template <typename E>
 constexpr int score_tiles() {
   return sizeof(E) == 1 ? 4 : 2;
 }
-template <typename E, int G, bool PAGED>
-constexpr size_t ring_scored_bytes() {
-  if constexpr (ring_scored<E, G, PAGED>()) return ring_bytes<E>(score_tiles<E>());
-  return 0;
+// LDS of the rings, after the scores (0 if the step has none).
+template <typename E>
+constexpr size_t score_ring_bytes(bool ring) {
+  return ring ? ring_bytes<E>(score_tiles<E>()) : 0;
 }
 
 // The score tile on the matrix cores: s[h*pitch + j] = scale_log2 * <q_h,
