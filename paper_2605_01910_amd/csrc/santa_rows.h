@@ -213,7 +213,7 @@ __device__ __forceinline__ void wave_claims_gather(const FusedArgs &a, int b, in
 // Claim r takes the key #{j : a P_j <= tau_r - lo} of the split's LDS CDF
 // (App. A, clamped to the split) with weight 1.  Returns the head's partial
 // sum O_h = sum_j c_{h,j} V_j (Sec. 2) in lanes 0..15.
-template <typename E, bool PAGED, int MODE>
+template <typename E, bool PAGED, int MODE, bool AHEAD>
 __device__ __forceinline__ void row_head_value(const FusedArgs &a, const HeadClaim &c,
                                                const float *uh, const float (&ureg)[4], bool staged,
                                                const float *Ph, int nrows, int start, int b,
@@ -250,37 +250,44 @@ __device__ __forceinline__ void row_head_value(const FusedArgs &a, const HeadCla
     rlo = __builtin_amdgcn_readlane(n, 0);
     rhi = __builtin_amdgcn_readlane(n, 1);
   }
-  // two heads per wave (G = 8): the uniforms are in memory, and each pass of 64
-  // claims fetches the next pass's, so that their latency runs under this
-  // pass's searches and gathers (6 ragged paged sequences up to 20011 keys, S =
-  // 1000: 92.9 -> 91.4 us; 16 of them: 192.4 -> 188.6 us, cold 251 -> 244)
-  const bool fetch = MODE == kStrat && !staged;
-  float unext = 0.0f;
-  if (fetch && rlo + lane < rhi) unext = uh[rlo + lane];
-  auto claim = [&](int r, bool ok) {
-    float ur = ureg[0];
-    if (fetch) {
-      ur = unext;
-      if (r + 64 < rhi) unext = uh[r + 64];
-    }
-    if (MODE != kSys && regs) {  // u_r (T_r) from lane r % 64 (every lane takes part)
-      const int src = r & 63, k = (r >> 6) & 3;
-      const float v0 = __shfl(ureg[0], src), v1 = __shfl(ureg[1], src);
-      const float v2 = __shfl(ureg[2], src), v3 = __shfl(ureg[3], src);
-      ur = k == 0 ? v0 : (k == 1 ? v1 : (k == 2 ? v2 : v3));
-    }
-    int j = 0;
-    if (ok) {
-      const float tau = MODE == kIid ? (regs ? ur : uh[r]) * c.Z
-                                     : threshold(r, (MODE == kStrat && !regs && !fetch) ? uh[r] : ur,
-                                                 a.invS, c.Z);
-      const int pos = lds_cdf_count(Ph, nrows, c.a, tau - c.lo);
-      j = pos < nrows ? pos : nrows - 1;
-      if (a.idx_out) a.idx_out[rowq * a.S + r] = start + j;
-    }
-    return Claim{j, 1.0f};
+  auto draw = [&](int r, float tau) {  // the key of claim r
+    const int pos = lds_cdf_count(Ph, nrows, c.a, tau - c.lo);
+    const int j = pos < nrows ? pos : nrows - 1;
+    if (a.idx_out) a.idx_out[rowq * a.S + r] = start + j;
+    return j;
   };
-  wave_claims_gather<E, PAGED>(a, b, kvh, start, rlo, rhi, claim, keyl, cntl, acc);
+  if constexpr (AHEAD) {
+    // stratified, two heads per wave (G = 8): the uniforms are in memory, and
+    // each pass of 64 claims fetches the next pass's, so that their latency
+    // runs under this pass's searches and gathers (16 ragged paged sequences
+    // up to 20011 keys, S = 1000: 192.4 -> 188.6 us, after a cache flush 251 ->
+    // 244).  A form of its own: as a run-time choice it cost the kernels that
+    // hold their uniforms in registers two of their 64, spilled to scratch
+    // (batch 1, G = 4: 19.55 -> 19.76 us)
+    float unext = rlo + lane < rhi ? uh[rlo + lane] : 0.0f;
+    auto claim = [&](int r, bool ok) {
+      const float ur = unext;
+      if (r + 64 < rhi) unext = uh[r + 64];
+      return Claim{ok ? draw(r, threshold(r, ur, a.invS, c.Z)) : 0, 1.0f};
+    };
+    wave_claims_gather<E, PAGED>(a, b, kvh, start, rlo, rhi, claim, keyl, cntl, acc);
+  } else {
+    auto claim = [&](int r, bool ok) {
+      float ur = ureg[0];
+      if (MODE != kSys && regs) {  // u_r (T_r) from lane r % 64 (every lane takes part)
+        const int src = r & 63, k = (r >> 6) & 3;
+        const float v0 = __shfl(ureg[0], src), v1 = __shfl(ureg[1], src);
+        const float v2 = __shfl(ureg[2], src), v3 = __shfl(ureg[3], src);
+        ur = k == 0 ? v0 : (k == 1 ? v1 : (k == 2 ? v2 : v3));
+      }
+      int j = 0;
+      if (ok)
+        j = draw(r, MODE == kIid ? (regs ? ur : uh[r]) * c.Z
+                                 : threshold(r, (MODE == kStrat && !regs) ? uh[r] : ur, a.invS, c.Z));
+      return Claim{j, 1.0f};
+    };
+    wave_claims_gather<E, PAGED>(a, b, kvh, start, rlo, rhi, claim, keyl, cntl, acc);
+  }
 }
 
 // S2ANTA-flash value stage of head h in split t, by one wave (Sec. 3.3; App.
@@ -447,8 +454,9 @@ __attribute__((amdgpu_waves_per_eu(row_waves<E, G, PAGED>()))) void k_row_sample
       __builtin_amdgcn_wave_barrier();
       uh = P + G * pitch + h * a.S;
     }
-    row_head_value<E, PAGED, MODE>(a, c, uh, ureg, G <= 4, P + h * pitch, nrows, start, b, kvh,
-                                   row0 + h, keyl[wave], cntl[wave], acc);
+    row_head_value<E, PAGED, MODE, (MODE == kStrat && G > 4)>(a, c, uh, ureg, G <= 4, P + h * pitch,
+                                                              nrows, start, b, kvh, row0 + h,
+                                                              keyl[wave], cntl[wave], acc);
     if (lane < 16) {
       float2 *d = reinterpret_cast<float2 *>(part + h * kHeadDim + lane * 8);
 #pragma unroll

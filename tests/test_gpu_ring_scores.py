@@ -38,3 +38,24 @@ def test_ring_scores_edges(cache, G, path, kernels, kind):
         again, idx2, _ = run(w, dw=dw)
     assert np.array_equal(out, again) and np.array_equal(idx, idx2)
     log(f"[ring scores {cache} G={G} {path} {kind}] {check_sampled(w, out, idx)}")
+
+
+@pytest.mark.parametrize("S_", [65, 129, 1000])
+@pytest.mark.parametrize("cache", ["bf16", "page16", "fp8"])
+def test_more_claims_than_lanes(cache, S_):
+    """Groups of eight, stratified: a split that takes more than 64 claims of a head goes through
+    several passes, each fetching the next one's uniforms.  The row of 40 keys takes all S in one
+    split; 65 and 129 leave one claim to the last pass."""
+    over = dict(B=4, Hkv=2, Hq=16, n=2600, ctx_len=[0, 40, 700, 2600], kind="stratified", S=S_)
+    if cache == "fp8":
+        over["kv_dtype"] = "fp8"
+    if cache == "page16":
+        over.update(paged=True, page_size=16)
+    w = make_workload(2, seed=80, **over)
+    dw = DeviceWorkload(w)
+    _poison(dw, w)
+    with S.options("rows", splits=3):
+        plan = S.santa_plan_info(dw.shape, dw.kv, w.S, KIND_CODE["stratified"])
+        assert plan["kernels"] == "k_row_sampled", plan
+        out, idx, _ = run(w, dw=dw)
+    log(f"[claims {cache} S={S_}] {check_sampled(w, out, idx)}")
