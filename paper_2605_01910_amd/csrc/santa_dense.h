@@ -324,15 +324,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   __shared__ int rank_lds;
   const int T = a.T, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rowkv = blockIdx.x / T, t = blockIdx.x % T;
+  // Split-major, each split's rows turned by one: the splits that hold keys
+  // come first, whatever share of the cache's capacity the rows fill, and a
+  // row's splits alternate over the XCDs (workgroup w runs on XCD w % 8).
+  // With the splits of a row in a run and T a multiple of 8, the first splits
+  // of short rows all ran on the same few XCDs (batch 16 of 500 keys in a
+  // cache of 32768: 126 us, so 16; of 8000: 138, so 90); full rows gain by the
+  // heads of a token read together (batch 16 at 32k keys: 346 -> 328).
+  const int nrk = a.B * a.Hkv, t = blockIdx.x / nrk, rowkv = (blockIdx.x % nrk + t) % nrk;
   const int b = rowkv / a.Hkv, kvh = rowkv % a.Hkv;
   const int64_t row0 = (int64_t)b * a.Hq + kvh * G;
   QE<E> *out = static_cast<QE<E> *>(a.out);
   const int L = seq_len(a.kv, b);
   int Ls, Tb;
   split_geometry(L, T, Ls, Tb);
-  if (Ls < a.Ls) {  // short rows take fewer splits of at least a.Ls keys, not T tiny ones
-    Ls = a.Ls;
+  if (Ls < a.Ls) {  // short rows: not T tiny splits, but as many as fill the chip
+    Ls = max(Ls, min(a.Ls, (((L + a.fill - 1) / a.fill) + kAlign - 1) & ~(kAlign - 1)));
     Tb = (L + Ls - 1) / Ls;
   }
   if (t >= Tb) {
@@ -488,7 +495,14 @@ hipError_t launch_dense_e(const Plan &p, const KvView &kv, const void *q, float 
     const bool ap = kv.k_new != nullptr;
     if constexpr (sizeof(E) <= 2) {
       if (dense_streams(p, PG)) {
+        // Rows of fewer than 512 T keys take fewer splits than T, of up to 512
+        // keys, but together at least two workgroups per CU if the row count
+        // allows it.  Splits of 512 keys throughout left batch 2 of 500 keys
+        // (capacity 65536) at 20 us for 8; one workgroup per CU is level or
+        // better in full caches of short rows and 10 % behind on ragged ones (4
+        // paged sequences of 500 to 9000 keys 21.6 us for 18.2).
         args.Ls = std::min(p.Ls, 512);
+        args.fill = (512 + p.B * p.Hkv - 1) / (p.B * p.Hkv);
         const void *fn = reinterpret_cast<const void *>(&k_dense_stream<E, G, PG>);
         if constexpr (sizeof(E) == 2)  // (an FP8 cache takes no append)
           if (ap) fn = reinterpret_cast<const void *>(&k_dense_stream<E, G, PG, true>);

@@ -78,7 +78,9 @@ struct FusedArgs {
   int tile_log2;  // flash: log2 of the tile length (16 .. kSplitMax keys)
   int S_tile;     // flash: samples per tile and head
   int Tmax;       // flash: tiles of the longest row, ceil(n_k / tile)
-  int Ls;         // scheduled sampled path: keys per split of every row (multiple of 64)
+  int Ls;         // scheduled sampled path: keys per split of every row (multiple of 64);
+                  // k_dense_stream: longest split that short rows are given
+  int fill;       // k_dense_stream: splits per row that fill the chip
   int direct;     // scheduled sampled path: every wave polls the row's statistics mailbox
 };
 
