@@ -68,15 +68,29 @@ struct Plan {
 
 // The dense step of 16-bit and FP8 caches takes k_dense_stream on grids (KV
 // rows x splits) of several workgroups per CU, where its continuous stream
-// counts (us, this kernel / k_fused_dense, 32k keys unless said): batch 4 98.9
-// / 112.4, batch 16 350 / 374, head-major 344 / 351, FP8 227 / 238, groups of
-// 8 at batch 4 114 / 147, 24 ragged paged sequences up to 16k 175 / 210.  At
-// two workgroups per CU a contiguous cache streams as fast through registers
+// counts (us, this kernel / k_fused_dense, 32k keys unless said): batch 4 95 /
+// 110, batch 16 328 / 365 (G = 1 318 / 344, G = 8 356 / 437), head-major 333 /
+// 344, FP8 211 / 237, groups of 8 at batch 4 107 / 147, 24 ragged paged
+// sequences up to 16k 164 / 199; grids of 520 to 1024: batch 3 74.3 / 74.6, 5
+// at 16k 64 / 69, 9 at 8k 56 / 65 (FP8 42 / 50).
+// At two workgroups per CU a contiguous cache streams as fast through registers
 // and the deeper rings only queue up (batch 1 34.7 / 30.4, batch 2 55.1 / 52.1,
 // batch 8 at 8k 54.2 / 50.7); a paged one does not (4 ragged sequences up to
-// 9000 keys 23.9 / 31.7).
+// 9000 keys 20 / 28) unless its splits are of 64 keys, one tile per wave:
+// batch 1 of 4000 keys G = 2 13.1 / 13.7, G = 4 13.1 / 14.6, but G = 1 13.7 /
+// 12.5 and G = 8 20.2 / 19.2.
+// Rows in one split (more than 512 rows of up to 1024 keys) are too short for
+// a stream where the arithmetic is little: batch 128, G = 1, contiguous, 64
+// keys 13.1 / 11.9, 256 30.6 / 26.6, 400 37.8 / 38.4; FP8 64 12.0 / 11.0, 256
+// 21.3 / 17.2, 1000 52.7 / 48.8 (G = 2 13.2 / 15.5, 23.4 / 21.5, 55.2 / 53.4);
+// paged 16 keys 12.2 / 10.6 (FP8 64 12.5 / 12.7, batch 300 32.1 / 29.6).
 inline bool dense_streams(const Plan &p, bool paged) {
-  return p.elem != 1 && (int64_t)p.B * p.Hkv * p.T > (paged ? 256 : 512);
+  const int64_t grid = (int64_t)p.B * p.Hkv * p.T;
+  if (p.elem == 1 || grid <= (paged ? 256 : 512)) return false;
+  if (grid <= 512) return p.Ls > 64 || p.G == 2 || p.G == 4;
+  if (p.T == 1 && p.G == 1) return p.Ls > (paged ? 64 : p.elem == 2 ? 1024 : 256);
+  if (p.T == 1 && p.G == 2 && p.elem == 2 && !paged) return p.Ls <= 64;
+  return true;
 }
 
 // KV cache as the kernels see it (see santa_kv_t for the addressing rules).

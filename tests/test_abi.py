@@ -202,3 +202,30 @@ def test_flash_path_choice():
     for B in (1, 4, 16):
         need = ws_size(_shape(B=B), _kv(), 0, flash)
         assert _plan(_shape(B=B), _kv(), 0, flash)["workspace"] <= need
+
+
+def test_dense_kernel_choice():
+    """The dense step's kernel by grid, cache and group: k_dense_stream for 16-bit and FP8 caches above
+    two workgroups per CU (paged: above one, if the splits hold more than one tile per wave or the
+    group is 2 or 4); rows in one split keep k_fused_dense where a stream is too short to pay."""
+    dense, stream, fused = S.SANTA_KIND_DENSE, "k_dense_stream", "k_fused_dense"
+
+    def kernel(B, n, G=4, Hkv=8, paged=False, fp8=False, dtype=0, splits=0):
+        kv = _kv(n=n, bt=16, ps=16, mp=-(-n // 16)) if paged else _kv(n=n)
+        if fp8:
+            kv.kv_dtype, kv.k_scale, kv.v_scale = S.SANTA_KV_FP8_E4M3, 16, 16
+        return _plan(_shape(B=B, Hq=Hkv * G, Hkv=Hkv, dtype=dtype), kv, 1, dense, splits=splits)["kernels"]
+
+    # contiguous: 512 workgroups and 768
+    assert kernel(1, 32768) == kernel(2, 32768) == fused and kernel(3, 32768) == stream
+    assert kernel(3, 32768, fp8=True) == stream and kernel(3, 32768, dtype=1) == fused
+    # paged: 256, 264 (128-key splits), 504 of 64 keys
+    assert kernel(1, 2048, paged=True) == fused and kernel(1, 4224, paged=True, splits=33) == stream
+    assert [kernel(1, 4000, G, paged=True) for G in (1, 2, 4, 8)] == [fused, stream, stream, fused]
+    # rows in one split: 65 sequences of 8 KV heads
+    assert [kernel(65, n, 1) for n in (64, 256, 257)] == [fused, fused, stream]
+    assert [kernel(65, n, 1, paged=True) for n in (64, 65)] == [fused, stream]
+    assert [kernel(65, n, 1, fp8=True) for n in (64, 1024)] == [fused, fused]
+    assert [kernel(65, n, 2, fp8=True) for n in (64, 65)] == [stream, fused]
+    assert kernel(65, 1100, 1, fp8=True) == stream  # two splits
+    assert kernel(65, 64, 4) == kernel(65, 64, 8) == kernel(65, 64, 2) == stream
