@@ -339,7 +339,8 @@ __device__ __forceinline__ void row_head_flash(const FusedArgs &a, const float *
 // base on and empties the mailbox.  Otherwise, where waiting workgroups share
 // CUs with streaming ones, thread 0 polls the counter: two arrivals per
 // split, after the statistics and after the partial sums.
-template <typename E, int G, bool PAGED, int MODE, bool APPEND = false, bool USTAGE = false>
+// RING: scores on the matrix cores (ring_scores, chosen by rows_ring).
+template <typename E, int G, bool PAGED, int MODE, bool APPEND, bool USTAGE, bool RING>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(row_waves<E, G, PAGED>()))) void k_row_sampled(FusedArgs a) {
   static_assert(MODE == kSys || MODE == kStrat || (MODE == kIid && G <= 4),
@@ -375,7 +376,7 @@ __attribute__((amdgpu_waves_per_eu(row_waves<E, G, PAGED>()))) void k_row_sample
 
   // 1. scores of the G heads into LDS, split max, split CDF and statistics
   const float ksc = kv_scales<E>(a.kv, b, kvh, a.Hkv).x;  // FP8 cache: K scale
-  if constexpr (ring_scored_rows<E, G, PAGED>()) {
+  if constexpr (RING) {
     ring_scores<E, G, PAGED>(a.kv, b, kvh, start, nrows, static_cast<const QE<E> *>(a.q), row0,
                              a.scale_log2 * ksc, P, pitch, P + G * pitch, mtmp, mh);
   } else {
@@ -669,30 +670,39 @@ hipError_t launch_rows_e(const Plan &p, const KvView &kv, const void *q, float s
     constexpr int G = decltype(gc)::value;
     constexpr bool PG = decltype(paged)::value;
     const bool ap = kv.k_new != nullptr;
+    auto form = [&](auto ringc) -> const void * {
+      constexpr bool R = decltype(ringc)::value;
+      auto one = [&](auto modec, auto stagec) -> const void * {
+        constexpr int M = decltype(modec)::value;
+        constexpr bool U = decltype(stagec)::value;
+        return ap ? reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, M, true, U, R>)
+                  : reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, M, false, U, R>);
+      };
+      const std::integral_constant<int, kSys> sys{};
+      const std::integral_constant<int, kStrat> strat{};
+      const std::false_type no{};
+      if constexpr (G <= 4) {
+        const std::integral_constant<int, kIid> iid{};
+        const std::true_type staged{};  // uniforms or thresholds staged in LDS
+        if (mode == kIid) return args.ustage ? one(iid, staged) : one(iid, no);
+        if (mode == kStrat && args.ustage) return one(strat, staged);
+      }
+      return mode == kStrat ? one(strat, no) : mode == kSys ? one(sys, no) : nullptr;
+    };
+    bool ring = false;
     const void *fn = nullptr;
-    if (mode == kStrat)
-      fn = ap ? reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kStrat, true>)
-              : reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kStrat>);
-    else if (mode == kSys)
-      fn = ap ? reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kSys, true>)
-              : reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kSys>);
-    if constexpr (G <= 4) {
-      if (mode == kIid)
-        fn = args.ustage
-                 ? (ap ? reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kIid, true, true>)
-                       : reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kIid, false, true>))
-                 : (ap ? reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kIid, true>)
-                       : reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kIid>));
-      if (mode == kStrat && args.ustage)  // uniforms staged in LDS
-        fn = ap ? reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kStrat, true, true>)
-                : reinterpret_cast<const void *>(&k_row_sampled<E, G, PG, kStrat, false, true>);
+    if constexpr (sizeof(E) <= 2 && (G == 8 || (PG && sizeof(E) == 2))) {
+      ring = rows_ring(p, PG);
+      fn = ring ? form(std::true_type{}) : form(std::false_type{});
+    } else {
+      fn = form(std::false_type{});
     }
     if (!fn) return hipErrorInvalidValue;
     void *params[] = {&args};
     // direct grids of G = 4 merge through LDS (merge_group4_lds: T partials,
     // at most 128 KiB, within the 160 KiB of a CU); staged stratified
     // uniforms (at most 2048 per head) follow the split CDFs
-    const size_t lds = std::max({(size_t)G * kSplitMax * 4 + score_ring_bytes<E>(ring_scored_rows<E, G, PG>()),
+    const size_t lds = std::max({(size_t)G * kSplitMax * 4 + score_ring_bytes<E>(ring),
                                  args.direct && G == 4 ? (size_t)p.T * G * kHeadDim * 4 : 0,
                                  args.ustage ? (size_t)G * (kSplitMax + p.S) * 4 : 0});
     const CallTimer tm = call_timer();

@@ -593,27 +593,17 @@ __device__ __forceinline__ void block_max_heads(float (&mx)[G], float *tmp, floa
   __syncthreads();
 }
 
-// Whether a sampled step's key stream goes through the matrix cores
-// (ring_scores) rather than through registers (score_tile) on every grid:
-// groups of eight, where score_tile needs 90 vector instructions per 4 keys
-// and 143 registers (us, score_tile / ring_scores, S = 256, 32k keys: batch 1
-// contiguous 40.7 / 29.9, paged 48.6 / 30.8, FP8 41.2 / 27.7; batch 16 296 /
-// 279, 352 / 297, FP8 263 / 139).
+// Whether the two-launch step's key stream goes through the matrix cores
+// (ring_scores) rather than through registers (score_tile): groups of eight,
+// where score_tile needs 90 vector instructions per 4 keys and 143 registers
+// (us, score_tile / ring_scores: 32 ragged paged sequences up to 32k keys 370 /
+// 289, FP8 batch 16 263 / 139, batch 300 of 300 keys 164 / 135).  Paged caches
+// of smaller groups gain 0.5 to 1.4 % (64 sequences up to 65536 keys), less
+// than it is worth to have a paged cache draw other keys, at ties of rounding,
+// than a contiguous one.  The scheduled step has a rule of its own (rows_ring).
 template <typename E, int G>
 constexpr bool ring_scored() {
   return sizeof(E) <= 2 && G == 8;
-}
-// The scheduled kernel (k_row_sampled) also scores paged 16-bit caches of
-// smaller groups so: their page lookups leave score_tile half the waves of a
-// contiguous stream (batch 1, G = 4, 32k keys: 25.0 / 18.5 us).  The two-launch
-// stream of these keeps score_tile: 64 sequences up to 65536 keys gain 0.5 to
-// 1.4 % (G = 1 to 4), less than it is worth to have a paged cache draw other
-// keys, at ties of rounding, than a contiguous one.  Contiguous caches of
-// smaller groups keep score_tile at eight waves per SIMD (batch 16 at 32k: 187
-// us, 5.8 TB/s), which holds as many loads in flight as the rings.
-template <typename E, int G, bool PAGED>
-constexpr bool ring_scored_rows() {
-  return ring_scored<E, G>() || (PAGED && sizeof(E) == 2);
 }
 // Tiles of each wave's ring: 32 KB per workgroup, so that it and the scores of
 // G heads leave room for two (G = 8) or three workgroups per CU.

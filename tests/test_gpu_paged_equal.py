@@ -9,7 +9,7 @@ import torch
 
 from oracle import oracle as O
 from paper_2605_01910_amd import santa as S
-from tests.gpu_util import KIND_CODE, DeviceWorkload, dev_elems, log, run
+from tests.gpu_util import KIND_CODE, DeviceWorkload, check_sampled, dev_elems, log, run
 from workload import make_workload
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +59,21 @@ def test_two_launch_draws_of_paged_and_contiguous_caches(G, kv):
         out_c, idx_c, _ = run(w, dw=contiguous(w, dw))
     log(f"[paged equal {kv} G={G}] {int((idx != idx_c).sum())} of {idx.size} draws differ")
     assert np.array_equal(idx, idx_c) and np.array_equal(out, out_c)
+
+
+@pytest.mark.parametrize("G,B", [(1, 130), (2, 100), (4, 100), (8, 80), (8, 100)])
+def test_scheduled_draws_beyond_one_resident_round(G, B):
+    """The scheduled step on grids of more workgroups than the matrix-core form holds resident (G =
+    8: 640 and 800 of one split a row, where the register form takes one round and two, the other
+    two and two): paged and contiguous caches draw the same, and what the oracle draws."""
+    lens = [(37 * i) % 200 + 1 for i in range(B - 1)] + [200]
+    w = make_workload(2, seed=84, B=B, Hkv=8, Hq=8 * G, n=200, ctx_len=lens, kind="stratified", S=70,
+                      paged=True, page_size=16)
+    dw = DeviceWorkload(w)
+    plan = S.santa_plan_info(dw.shape, dw.kv, w.S, KIND_CODE["stratified"])
+    assert (plan["kernels"], plan["splits"]) == ("k_row_sampled", 1), plan
+    out, idx, _ = run(w, dw=dw)
+    out_c, idx_c, _ = run(w, dw=contiguous(w, dw))
+    assert np.array_equal(idx, idx_c) and np.array_equal(out, out_c)
+    rows = list(range(0, B * w.Hq, 61))
+    log(f"[beyond one round G={G} B={B}] {check_sampled(w, out, idx, rows=rows)}")
