@@ -33,7 +33,7 @@ def _differences(q, kv_of, B, kernel):
     return torch.log2(p / (1 - p))
 
 
-@pytest.mark.parametrize("cache,G", [("bf16", 1), ("bf16", 4), ("bf16", 8), ("fp8", 4)])
+@pytest.mark.parametrize("cache,G", [("bf16", 2), ("bf16", 4), ("bf16", 8), ("fp8", 4)])
 def test_matrix_core_scores_round_no_worse_than_vector_scores(cache, G):
     g = torch.Generator(device="cuda").manual_seed(5)
     n_seq = ROWS // HKV
