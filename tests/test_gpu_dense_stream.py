@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from paper_2605_01910_amd import santa as S
-from tests.gpu_util import DeviceWorkload, check_dense, log, run
+from tests.gpu_util import DeviceWorkload, check_dense, current_rows, log, run
 from workload import make_workload
 
 pytestmark = pytest.mark.gpu
@@ -60,6 +60,7 @@ def test_dense_stream_scores_of_minus_infinity():
     w = make_workload(2, seed=78, B=9, Hkv=8, Hq=32, n=512, kind="systematic", S=16)
     dw = DeviceWorkload(w)
     with S.options("auto", splits=8):
+        assert S.santa_plan_info(dw.shape, dw.kv, 1, S.SANTA_KIND_DENSE)["kernels"] == "k_dense_stream"
         ref, _, _ = run(w, "dense", dw=dw)
         k = dw.k.clone()
         dw.q[..., 0] = 1.0               # one positive feature for every head
@@ -71,3 +72,45 @@ def test_dense_stream_scores_of_minus_infinity():
     s = torch.einsum("bkgd,bnkd->bkgn", q.view(9, 8, 4, 128), k[:, keep]) * w.scale
     o = torch.einsum("bkgn,bnkd->bkgd", torch.softmax(s, -1), v[:, keep]).reshape(-1, 128).numpy()
     assert np.all(np.isfinite(ref)) and np.abs(out - o).max() <= 2e-2
+
+
+# the last key: the only one, the last or first of a tile, of a split of 64 (128, 320) keys, neither
+APPEND_SHORT = [1, 16, 17, 64, 65, 129, 449, 490, 500]
+APPEND_LONG = [1, 128, 129, 256, 257, 700, 1025, 2561, 2600]
+
+
+@pytest.mark.parametrize("lens", [APPEND_SHORT, APPEND_LONG], ids=["short", "long"])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("cache", ["nhd", "hnd", "page4", "page16", "page64"])
+def test_dense_stream_append(cache, G, lens):
+    """The current token's rows, stored by the call and then read through LDS copies: the cache holds
+    NaN there before, and past it.  Head-major and sequence-major caches and pages."""
+    Hkv, n = 8, max(lens)
+    over = dict(B=len(lens), Hkv=Hkv, Hq=Hkv * G, n=n, ctx_len=lens, kind="systematic", S=16)
+    if cache.startswith("page"):
+        over.update(paged=True, page_size=int(cache[4:]))
+    w = make_workload(2, seed=85, **over)
+    dw = DeviceWorkload(w, "hnd" if cache == "hnd" else "nhd")
+    rows = current_rows(dw, w)
+    k_new = torch.stack([k.clone() for k, _ in rows]).contiguous()
+    v_new = torch.stack([v.clone() for _, v in rows]).contiguous()
+    if cache == "hnd":
+        for b, L in enumerate(lens):
+            dw.k[b, :, L:] = dw.v[b, :, L:] = float("nan")
+    else:
+        _poison(dw, w)
+    kinds = {}
+    for append in (False, True):
+        if append:
+            for k, v in rows:
+                k.fill_(float("nan"))
+                v.fill_(float("nan"))
+            dw.kv.k_new, dw.kv.v_new = k_new.data_ptr(), v_new.data_ptr()
+        with S.options("auto", splits=8 if lens is APPEND_SHORT else 12):
+            plan = S.santa_plan_info(dw.shape, dw.kv, 1, S.SANTA_KIND_DENSE)
+            assert plan["kernels"] == "k_dense_stream", plan
+            kinds[append], _, _ = run(w, "dense", dw=dw)
+    for b, (k, v) in enumerate(rows):
+        assert torch.equal(k, k_new[b]) and torch.equal(v, v_new[b]), f"cache row of sequence {b}"
+    assert np.array_equal(kinds[False], kinds[True])
+    log(f"[dense stream append {cache} G={G}] {check_dense(w, kinds[True])}")
