@@ -1,5 +1,5 @@
-// santa_dense.h -- the exact dense step and the S2ANTA-flash step
-// (k_fused_dense; see santa_fused.h).
+// santa_dense.h -- the exact dense step (k_dense_stream and k_fused_dense; see
+// santa_fused.h) and the S2ANTA-flash step on k_fused_dense.
 #pragma once
 
 #include "santa_fused.h"
@@ -492,9 +492,18 @@ hipError_t launch_dense_e(const Plan &p, const KvView &kv, const void *q, float 
   return with_g_paged(p.G, kv.bt != nullptr, [&](auto gc, auto paged) -> hipError_t {
     constexpr int G = decltype(gc)::value;
     constexpr bool PG = decltype(paged)::value;
-    const bool ap = kv.k_new != nullptr;
+    constexpr bool AP = sizeof(E) > 1;  // an FP8 cache takes no append
+    const bool ap = AP && kv.k_new != nullptr;
+    const int rows = p.B * p.Hkv;
+    const size_t lds = (size_t)fused_dense_floats(G, kSplitMax, p.T) * 4;
+    const void *res = ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true, false, AP>)
+                         : reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true>);
+    // k_fused_dense beyond one resident round: float32, and the short rows
+    // that dense_streams leaves to it
+    constexpr bool many = sizeof(E) == 4 || G == 1 || (G == 2 && sizeof(E) == 1);
+    auto resident = [&] { return rows * p.T <= capacity_of(res, lds); };
     if constexpr (sizeof(E) <= 2) {
-      if (dense_streams(p, PG)) {
+      if (dense_streams(p, PG) || (!many && !resident())) {
         // Rows of fewer than 512 T keys take fewer splits than T, of up to 512
         // keys, but together at least two workgroups per CU if the row count
         // allows it.  Splits of 512 keys throughout left batch 2 of 500 keys
@@ -502,28 +511,24 @@ hipError_t launch_dense_e(const Plan &p, const KvView &kv, const void *q, float 
         // better in full caches of short rows and 10 % behind on ragged ones (4
         // paged sequences of 500 to 9000 keys 21.6 us for 18.2).
         args.Ls = std::min(p.Ls, 512);
-        args.fill = (512 + p.B * p.Hkv - 1) / (p.B * p.Hkv);
-        const void *fn = reinterpret_cast<const void *>(&k_dense_stream<E, G, PG>);
-        if constexpr (sizeof(E) == 2)  // (an FP8 cache takes no append)
-          if (ap) fn = reinterpret_cast<const void *>(&k_dense_stream<E, G, PG, true>);
+        args.fill = (512 + rows - 1) / rows;
+        const void *fn = ap ? reinterpret_cast<const void *>(&k_dense_stream<E, G, PG, AP>)
+                            : reinterpret_cast<const void *>(&k_dense_stream<E, G, PG>);
         void *params[] = {&args};
         const CallTimer tm = call_timer();
-        return hipExtLaunchKernel(fn, dim3(p.B * p.Hkv * p.T), dim3(kThreads), params,
+        return hipExtLaunchKernel(fn, dim3(rows * p.T), dim3(kThreads), params,
                                   dense_lds_bytes<E>(G, p.T), st, tm.start, tm.stop, 0);
       }
     }
-    const size_t lds = (size_t)fused_dense_floats(G, kSplitMax, p.T) * 4;
-    const void *res = ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true, false, true>)
-                         : reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true>);
-    const int rows = p.B * p.Hkv;
-    if (rows * p.T <= capacity_of(res, lds))  // one resident round
-      return launch_resident(res, p, args, lds, st);
-    void *params[] = {&args};
-    const CallTimer tm = call_timer();
-    return hipExtLaunchKernel(ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, false, false, true>)
-                                 : reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, false>),
-                              dim3(rows * p.T), dim3(kThreads), params, lds, st, tm.start, tm.stop,
-                              0);
+    if (resident()) return launch_resident(res, p, args, lds, st);
+    if constexpr (many) {
+      void *params[] = {&args};
+      const CallTimer tm = call_timer();
+      return hipExtLaunchKernel(ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, false, false, AP>)
+                                   : reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, false>),
+                                dim3(rows * p.T), dim3(kThreads), params, lds, st, tm.start, tm.stop, 0);
+    }
+    return hipErrorInvalidConfiguration;  // (not reached)
   });
 }
 
@@ -541,15 +546,16 @@ hipError_t launch_flash_e(const Plan &p, const KvView &kv, const void *q, float 
     constexpr int G = decltype(gc)::value;
     constexpr bool PG = decltype(paged)::value;
     const size_t lds = (size_t)fused_flash_floats(G, kSplitMax, p.T) * 4;
-    const bool ap = kv.k_new != nullptr;
-    const void *res = ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true, true, true>)
+    constexpr bool AP = sizeof(E) > 1;  // an FP8 cache takes no append
+    const bool ap = AP && kv.k_new != nullptr;
+    const void *res = ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true, true, AP>)
                          : reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, true, true>);
     const int rows = p.B * p.Hkv;
     if (rows * p.T <= capacity_of(res, lds))  // one resident round
       return launch_resident(res, p, args, lds, st);
     void *params[] = {&args};
     const CallTimer tm = call_timer();
-    return hipExtLaunchKernel(ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, false, true, true>)
+    return hipExtLaunchKernel(ap ? reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, false, true, AP>)
                                  : reinterpret_cast<const void *>(&k_fused_dense<E, G, PG, false, true>),
                               dim3(rows * p.T), dim3(kThreads), params, lds, st, tm.start, tm.stop,
                               0);

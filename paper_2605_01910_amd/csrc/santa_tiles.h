@@ -110,22 +110,6 @@ __device__ __forceinline__ int64_t row16_offset(const KvView &kv, const PageWin 
   }
 }
 
-// Element offset of token pos (feature 0) of the split whose page window is
-// pw, for lane-varying positions; every lane of the wave calls it (the page
-// comes from the lane that holds its entry), valid only where ok.
-template <bool PAGED>
-__device__ __forceinline__ int64_t row_offset_win(const KvView &kv, const PageWin &pw, int b, int kvh,
-                                                  int pos, bool ok) {
-  if constexpr (PAGED) {
-    if (kv.ps_log2 < 4) return ok ? row_offset<true>(kv, b, kvh, pos) : 0;
-    const int page = __shfl(pw.entry, (pos >> kv.ps_log2) - pw.p0);
-    return (int64_t)page * kv.sb + (int64_t)(pos & ((1 << kv.ps_log2) - 1)) * kv.sn +
-           (int64_t)kvh * kv.sh;
-  } else {
-    return row_offset<false>(kv, b, kvh, pos);
-  }
-}
-
 // 16 bytes at byte offset lb from p through a buffer resource (uniform base in
 // scalar registers, one 32-bit lane offset; no range limit is used).  The load
 // is non-temporal (cache-policy bit nt = 2): every key is read once per step,
