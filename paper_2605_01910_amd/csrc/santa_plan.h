@@ -96,27 +96,30 @@ inline bool dense_streams(const Plan &p, bool paged) {
 // The scheduled sampled step (k_row_sampled) scores on the matrix cores
 // (ring_scores) in groups of eight and on paged 16-bit caches.  Its rings leave
 // fewer workgroups per CU than the register form: 2 for 3 at G = 8, 3 (G = 1: 4)
-// for 4 to 6 at smaller G.  Workgroups that wait at a
-// row barrier or gather don't stream, so the smaller number shows where it
-// makes a difference (us, ring_scores / score_tile, S = 256):
+// for 4 to 6 at smaller G.  Workgroups that wait at a row barrier or gather
+// don't stream, so the smaller number shows where it takes a round more (us,
+// ring_scores / score_tile, S = 128 to 256, full rows unless said):
 // - G <= 4, paged: one resident round (G = 4, 32k keys: batch 1 18.5 / 25.0,
-//   batch 3, 768 workgroups, 41.9 / 44.6; batch 4 61.4 / 55.8, batch 16 157 /
-//   148, batch 300 of 500 keys 206 / 149; G = 1 batch 4 49.7 / 51.4, batch 5,
-//   1280 workgroups, 64.2 / 61.6).
+//   batch 3, 768 workgroups, 41.9 / 44.6; batch 4 61.5 / 55.7, 12 152 / 149;
+//   16 sequences of 800 to 8000 keys 53 / 48, 300 of 500 206 / 149; G = 2 level
+//   with that).  G = 1 also beyond two rounds, where the part of a round is
+//   small (batch 4 50.8 / 52.0; 5, 1280 workgroups, 64.6 / 62.1, 24 of 8000 keys
+//   73.0 / 71.3; 90 of 3000, 2160, 100.4 / 100.4, of 1500 to 3000 81 / 86, 60 of
+//   8000 161 / 164).
 // - G = 8: everywhere (batch 1 29.9 / 40.7, batch 16 279 / 296; paged 30.8 /
-//   48.6, 297 / 352; FP8 27.7 / 41.2) but in rows of one or two splits, which
+//   48.6, 297 / 352; FP8 27.7 / 41.2; 24 sequences of 3000 keys, 576 workgroups,
+//   62 / 66, of 300 to 3000 39 / 55) but in rows of one or two splits, which
 //   gather more than they stream, on grids that take a round more at two per CU
-//   than at three (batch 80 of 500 keys, 640 workgroups: 99 / 78, paged 149 /
-//   108, FP8 92 / 75; batch 128, 1024: 109 / 117; batch 300, 2400: 282 / 260;
-//   two splits of 1024: 40 sequences 96 / 85, 96 166 / 165, FP8 84 / 85, 136 /
-//   155), and bfloat16 rows of up to four splits on 513 to 768 (20 sequences
-//   of 4096 keys 77.7 / 75.6, paged 97 / 91; 5 of 16384 66.4 / 67.5, 71.8 / 77.0).
+//   than at three (80 sequences of 500 keys, 640 workgroups: 64 / 54, paged 78 /
+//   64, FP8 59 / 53; 128, 1024: 109 / 117; 300, 2400: 282 / 260; two splits: 36
+//   of 2000 73 / 69, paged 83 / 80, 46 of 860 to 1090 and S = 877 152 / 116; but
+//   FP8 64 / 70).
 inline bool rows_ring(const Plan &p, bool paged) {
   const int64_t grid = (int64_t)p.B * p.Hkv * p.T;
-  if (p.G < 8) return paged && p.elem == 0 && grid <= (p.G == 1 ? 1024 : 768);
-  const bool fp8 = p.elem == 2, one_round = grid > 512 && grid <= 768;
-  if (p.T == 1 || (p.T == 2 && !fp8)) return (grid + 511) / 512 <= (grid + 767) / 768;
-  return p.elem != 1 && !(one_round && p.T <= (fp8 ? 2 : 4));
+  if (p.G == 1) return paged && p.elem == 0 && (grid <= 1024 || grid > 2048);
+  if (p.G < 8) return paged && p.elem == 0 && grid <= 768;
+  if (p.T == 1 || (p.T == 2 && p.elem == 0)) return (grid + 511) / 512 <= (grid + 767) / 768;
+  return p.elem != 1;
 }
 
 // KV cache as the kernels see it (see santa_kv_t for the addressing rules).

@@ -77,3 +77,17 @@ def test_scheduled_draws_beyond_one_resident_round(G, B):
     assert np.array_equal(idx, idx_c) and np.array_equal(out, out_c)
     rows = list(range(0, B * w.Hq, 61))
     log(f"[beyond one round G={G} B={B}] {check_sampled(w, out, idx, rows=rows)}")
+
+
+def test_scheduled_draws_beyond_two_rounds_of_single_heads():
+    """G = 1 on paged caches scores on the matrix cores again beyond 2048 workgroups (2080 of one
+    split a row): what the oracle draws."""
+    B = 260
+    lens = [(37 * i) % 200 + 1 for i in range(B - 1)] + [200]
+    w = make_workload(2, seed=85, B=B, Hkv=8, Hq=8, n=200, ctx_len=lens, kind="stratified", S=70,
+                      paged=True, page_size=16)
+    dw = DeviceWorkload(w)
+    plan = S.santa_plan_info(dw.shape, dw.kv, w.S, KIND_CODE["stratified"])
+    assert (plan["kernels"], plan["splits"]) == ("k_row_sampled", 1), plan
+    out, idx, _ = run(w, dw=dw)
+    log(f"[beyond two rounds] {check_sampled(w, out, idx, rows=list(range(0, B * w.Hq, 61)))}")
