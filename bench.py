@@ -362,6 +362,7 @@ COMMON_SOURCES = ["include/santa.h", "csrc/santa_plan.h", "csrc/santa_device.h",
 FAMILY_SOURCES = {
     "k_fused_sampled": ["csrc/santa_sampled.h", "csrc/santa_sampled_*.hip"],
     "k_fused_dense": ["csrc/santa_dense.h", "csrc/santa_dense_*.hip"],
+    "k_dense_stream": ["csrc/santa_dense.h", "csrc/santa_dense_*.hip"],
     "k_stream_cdf + k_value_heads": ["csrc/santa_stream.h", "csrc/santa_stream_*.hip"],
     "k_bern_stream + k_value_heads": ["csrc/santa_stream.h", "csrc/santa_stream_*.hip"],
     "k_row_sampled": ["csrc/santa_rows.h", "csrc/santa_rows_*.hip"],

@@ -312,10 +312,11 @@ constexpr size_t dense_lds_bytes(int G, int T) {
 // scored; the four waves are joined once at the end.  The split publishes o_t
 // = sum exp2(s - m_t) V and (m_t, l_t); the row's last arrival merges O =
 // sum_t a_t o_t / sum_t a_t l_t, a_t = exp2(m_t - m*).  24 ragged
-// paged sequences of 512 to 16384 keys with the append: 207.2 -> 170.3 us (4.5
-// -> 5.5 TB/s; k_fused_dense's append variant spills).  Without the V arithmetic
-// it takes 164 us, without the merge 162; rings of three pairs take 241 us:
-// more than about 64 KB per CU in flight only queues up.
+// paged sequences of 512 to 16384 keys with the append: 207.2 (k_fused_dense,
+// whose append variant spills) -> 163.4 us (4.5 -> 5.7 TB/s).  At 170 us, with a
+// row's splits in a run, it took 164 us without the V arithmetic, 162 without
+// the merge and 241 with rings of three pairs: more than about 64 KB per CU in
+// flight only queues up.
 template <typename E, int G, bool PAGED, bool APPEND = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_dense_stream(FusedArgs a) {
   extern __shared__ __attribute__((aligned(16))) float dyn[];

@@ -371,7 +371,7 @@ __device__ __forceinline__ mf32x4 score_frag(const QFrag &qf, const unsigned (&r
 // LDS bank once.  The register form of the stream (score_tile: 16 lanes per
 // row, four dot2 per head and a 16-lane reduction) needs about 30 vector
 // instructions per 4 keys at G = 4 and 90 at G = 8; here 16 keys take 4 matrix
-// instructions and about 15 others, whatever G is.  Reading 1 GiB of keys in
+// instructions and about 30 others, whatever G is.  Reading 1 GiB of keys in
 // 1024-key splits: 160 us so, 171 us for the register form's loads alone, 200
 // us for loads straight into the operand layout (64-byte pieces of rows).
 // Rows past the end of the split repeat its last row, so they change no

@@ -2,14 +2,15 @@
 splits, against the CPU oracle: rows of 0 keys, of one key, of a tile plus or minus one, fewer
 tiles than waves, splits longer than the ring; pages of 4 to 64 keys, and groups of eight query
 heads on every cache.  What lies past a row's length is NaN: none of it may reach the output.
-Each of a key's 128 products is exact in float32 and their order of summation is all that differs
-between score stages, so the indices keep the oracle's 1e-5 band."""
+The products of a key are the same as on the vector units and their sums round no worse
+(test_gpu_score_rounding.py), so the indices keep the oracle's 1e-5 band."""
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_01910_amd import santa as S
-from tests.gpu_util import DeviceWorkload, KIND_CODE, check_sampled, log, run
+from tests.gpu_util import DeviceWorkload, KIND_CODE, check_sampled, current_rows, log, run
 from tests.test_gpu_dense_stream import _poison
 from workload import make_workload
 
@@ -59,3 +60,32 @@ def test_more_claims_than_lanes(cache, S_):
         assert plan["kernels"] == "k_row_sampled", plan
         out, idx, _ = run(w, dw=dw)
     log(f"[claims {cache} S={S_}] {check_sampled(w, out, idx)}")
+
+
+APPEND_LENS = [1, 16, 17, 64, 65, 1024, 1025, 2600]  # the last key: alone, last or first of a tile, of a split
+
+
+@pytest.mark.parametrize("path", ["rows", "two"])
+@pytest.mark.parametrize("cache,G", [("bf16", 8), ("page4", 8), ("page16", 8), ("page16", 4)])
+def test_ring_scores_append(cache, G, path):
+    """The current token's rows, stored by the call and then copied into the ring: the cache holds
+    NaN there before, and past it."""
+    over = dict(B=len(APPEND_LENS), Hkv=2, Hq=2 * G, n=max(APPEND_LENS), ctx_len=APPEND_LENS,
+                kind="stratified", S=100)
+    if "page" in cache:
+        over.update(paged=True, page_size=int(cache.split("page")[1]))
+    w = make_workload(2, seed=86, **over)
+    dw = DeviceWorkload(w)
+    rows = current_rows(dw, w)
+    k_new = torch.stack([k.clone() for k, _ in rows]).contiguous()
+    v_new = torch.stack([v.clone() for _, v in rows]).contiguous()
+    _poison(dw, w)
+    for k, v in rows:
+        k.fill_(float("nan"))
+        v.fill_(float("nan"))
+    dw.kv.k_new, dw.kv.v_new = k_new.data_ptr(), v_new.data_ptr()
+    with S.options(path, splits=3):
+        out, idx, _ = run(w, dw=dw)
+    for b, (k, v) in enumerate(rows):
+        assert torch.equal(k, k_new[b]) and torch.equal(v, v_new[b]), f"cache row of sequence {b}"
+    log(f"[ring append {cache} G={G} {path}] {check_sampled(w, out, idx)}")
