@@ -80,9 +80,14 @@ struct FusedArgs {
   int Tmax;       // flash: tiles of the longest row, ceil(n_k / tile)
   int Ls;         // scheduled sampled path: keys per split of every row (multiple of 64);
                   // k_dense_stream: longest split that short rows are given
+  int direct;     // scheduled sampled path: every wave polls the row's statistics mailbox (next
+                  // to Ls: one scalar load brings both at the kernel's start)
   int fill;       // k_dense_stream: splits per row that fill the chip
-  int direct;     // scheduled sampled path: every wave polls the row's statistics mailbox
 };
+// With a field between them the second load waited behind the length's: batch 1
+// of 1999 keys 9.5 -> 9.7 us, 12345 keys i.i.d. at batch 2 18.5 -> 18.8.
+static_assert(__builtin_offsetof(FusedArgs, direct) == __builtin_offsetof(FusedArgs, Ls) + sizeof(int),
+              "Ls and direct are loaded together");
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
